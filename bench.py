@@ -73,7 +73,7 @@ def kernel_source_hash():
 
 def short_kernel_name(name):
     """rocprofv3 kernel name -> the library's trace name."""
-    m = re.search(r"k_stream<[^>]*?::(\w+)Jobs", name)
+    m = re.search(r"k_(?:wgrad_)?stream<[^>]*?::(\w+)Jobs", name)
     if m:
         base = {"DownWgrad": "down_wgrad", "GateUpWgrad": "gateup_wgrad", "GateUpFwd": "gateup_fwd",
                 "DownFwd": "down_fwd", "DownDgrad": "down_dgrad_swiglu", "GateUpDgrad": "gateup_dgrad",

@@ -84,7 +84,8 @@ __global__ __launch_bounds__(256) void k_combine(const bf16_t* __restrict__ o, c
 // combine backward (independent work that would cost a launch of its own).
 struct PlanArgs {
   const int32_t* offsets = nullptr;
-  int E = 0, tpe0 = 0, tpe1 = 0;
+  int E = 0;
+  WgradTiles tiles;
   int32_t* plan = nullptr;
 };
 
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(256) void k_combine_bwd(const bf16_t* __restrict__ 
                                                      const int32_t* __restrict__ row_of, int T, int H, int k,
                                                      bf16_t* __restrict__ d_o, PlanArgs pa) {
   if (static_cast<int>(blockIdx.x) == cdiv(T, 4)) {  // the plan workgroup
-    build_wgrad_plan(pa.offsets, pa.E, pa.tpe0, pa.tpe1, pa.plan);
+    build_wgrad_plan(pa.offsets, pa.E, pa.tiles, pa.plan);
     return;
   }
   constexpr int kU = row_chunks<KT, 32>();
@@ -299,13 +300,14 @@ hipError_t launch_combine(const bf16_t* o, const float* gates, const int32_t* ro
 }
 
 hipError_t launch_combine_bwd(const bf16_t* dy, const float* gates, const int32_t* row_of, int T, int H, int k,
-                              bf16_t* d_o, hipStream_t s, const int32_t* offsets, int E, int F, int32_t* plan) {
+                              bf16_t* d_o, hipStream_t s, const int32_t* offsets, int E, int F, bool dw_f32,
+                              int32_t* plan) {
   PlanArgs pa;
   if (plan != nullptr) {
     pa.offsets = offsets;
     pa.E = E;
     pa.plan = plan;
-    wgrad_tiles_per_expert(H, F, pa.tpe0, pa.tpe1);
+    pa.tiles = wgrad_tiles(E, H, F, dw_f32);
   }
   {
     TraceScope trace_scope(K_COMBINE_BWD, s);

@@ -183,9 +183,9 @@ __device__ __forceinline__ void store4(void* out, int64_t idx, const f32x4& v) {
 // L2s.  Each tile is still computed whole by one workgroup: the schedule
 // changes no result.
 // k_wgrad_plan: the plan (wgrad_plan.hpp) as a launch of its own.
-__global__ __launch_bounds__(256) void k_wgrad_plan(const int32_t* __restrict__ offsets, int E, int tpe0, int tpe1,
+__global__ __launch_bounds__(256) void k_wgrad_plan(const int32_t* __restrict__ offsets, int E, WgradTiles tiles,
                                                     int32_t* __restrict__ plan) {
-  build_wgrad_plan(offsets, E, tpe0, tpe1, plan);
+  build_wgrad_plan(offsets, E, tiles, plan);
 }
 
 // Job i of this workgroup in weight gradient q (expert e, rows [m0, m0+BM),
@@ -766,7 +766,7 @@ int persistent_grid(Kernel kernel, int threads, int64_t max_tiles) {
 // Upper bound of the number of 128-row tiles over all experts.
 int max_row_tiles(int rows_cap, int E) { return cdiv(rows_cap, kRowTile) + E; }
 
-int wgrad_plan_ints(int E) { return E + 2 * (kPlanXcds + 1); }
+int wgrad_plan_ints(int E) { return plan_tall(E, 2); }
 
 
 // The dgrad of the down product runs 256-column tiles when F allows, else 128.
@@ -780,6 +780,12 @@ namespace {
 using Wide = Tile<128, 256, 1, 2, 4>;
 using Narrow = Tile<128, 128, 1, 2, 2>;
 using WideGU = Tile<128, 256, 2, 2, 4>;
+// Weight gradients with many tiles: 256 x 256 over 8 waves of 128 x 64, in
+// 32-deep steps.  A step has the MFMAs of a 128 x 256 x 64 one with two thirds
+// of its operand loads and three quarters of its fragment reads; both operands
+// are MN-contiguous, so a 32-deep stage still loads whole 512-byte row pieces.
+using Tall = Tile<256, 256, 1, 2, 4, 32>;
+using TallGU = Tile<256, 256, 2, 2, 4, 32>;
 
 template <bool A_KC, bool B_KC, class P>
 void run_stream(const P& prov, int64_t max_jobs, int kid, hipStream_t s) {
@@ -845,17 +851,51 @@ void gateup_dgrad(const ExpertArgs& a, const bf16_t* dg, const bf16_t* du, bf16_
                            tiles, K_GATEUP_DGRAD, s);
 }
 
+// The weight gradient of provider P on 128-row tiles, or on provider PT's
+// 256-row tiles where the plan says so (`tall`, written on the device).
+template <class PT, class P>
+__global__ __launch_bounds__(P::C::kThreads) void k_wgrad_stream(PT pt, P p, const int32_t* tall) {
+  static_assert(PT::C::kThreads == P::C::kThreads, "one block size for both tile heights");
+  __shared__ __attribute__((aligned(16))) char smem[std::max(stream_lds<PT>(), stream_lds<P>())];
+  if (uniform_load(tall) != 0) gemm_stream<typename PT::C, false, false>(pt, smem);
+  else gemm_stream<typename P::C, false, false>(p, smem);
+}
+
+template <class PT, class P>
+void run_wgrad(const PT& pt, const P& p, const int32_t* tall, int64_t max_jobs, int kid, hipStream_t s) {
+  auto k = k_wgrad_stream<PT, P>;
+  const int grid = persistent_grid(k, P::C::kThreads, max_jobs);
+  TraceScope trace_scope(kid, s);
+  hipLaunchKernelGGL(k, dim3(grid), dim3(P::C::kThreads), 0, s, pt, p, tall);
+}
+
 template <class C, bool F32>
 void down_wgrad(const ExpertArgs& a, const bf16_t* d_o, void* dw_down, hipStream_t s) {
   DownWgradJobs<C, F32> p{{}, a.offsets, a.wgrad_plan, a.act, d_o, a.E, a.H, a.F, dw_down};
-  run_stream<false, false>(p, static_cast<int64_t>(a.E) * (a.F / C::BM) * (a.H / C::BNS), K_DOWN_WGRAD, s);
+  const int64_t jobs = static_cast<int64_t>(a.E) * (a.F / C::BM) * (a.H / C::BNS);
+  if constexpr (!F32 && C::BN == Tall::BN) {
+    if (wgrad_tiles(a.E, a.H, a.F, F32).tall[0]) {
+      DownWgradJobs<Tall, F32> pt{{}, a.offsets, a.wgrad_plan, a.act, d_o, a.E, a.H, a.F, dw_down};
+      run_wgrad(pt, p, a.wgrad_plan + plan_tall(a.E, 0), jobs, K_DOWN_WGRAD, s);
+      return;
+    }
+  }
+  run_stream<false, false>(p, jobs, K_DOWN_WGRAD, s);
 }
 
 template <class C, bool F32>
 void gateup_wgrad(const ExpertArgs& a, const bf16_t* dg, const bf16_t* du, void* dw_gate, void* dw_up,
                   hipStream_t s) {
   GateUpWgradJobs<C, F32> p{{}, a.offsets, a.wgrad_plan, a.xp, dg, du, a.E, a.H, a.F, dw_gate, dw_up};
-  run_stream<false, false>(p, static_cast<int64_t>(a.E) * (a.H / C::BM) * (a.F / C::BNS), K_GATEUP_WGRAD, s);
+  const int64_t jobs = static_cast<int64_t>(a.E) * (a.H / C::BM) * (a.F / C::BNS);
+  if constexpr (!F32) {
+    if (wgrad_tiles(a.E, a.H, a.F, F32).tall[1]) {
+      GateUpWgradJobs<TallGU, F32> pt{{}, a.offsets, a.wgrad_plan, a.xp, dg, du, a.E, a.H, a.F, dw_gate, dw_up};
+      run_wgrad(pt, p, a.wgrad_plan + plan_tall(a.E, 1), jobs, K_GATEUP_WGRAD, s);
+      return;
+    }
+  }
+  run_stream<false, false>(p, jobs, K_GATEUP_WGRAD, s);
 }
 
 template <class C>
@@ -873,9 +913,18 @@ void gateup_wgrad_any(const ExpertArgs& a, const bf16_t* dg, const bf16_t* du, v
 
 }  // namespace
 
-void wgrad_tiles_per_expert(int H, int F, int& tpe_down, int& tpe_gu) {
-  tpe_down = H % 256 == 0 ? (F / Wide::BM) * (H / Wide::BNS) : (F / Narrow::BM) * (H / Narrow::BNS);
-  tpe_gu = (H / WideGU::BM) * (F / WideGU::BNS);
+WgradTiles wgrad_tiles(int E, int H, int F, bool dw_f32) {
+  WgradTiles t;
+  t.tpe[0] = H % 256 == 0 ? (F / Wide::BM) * (H / Wide::BNS) : (F / Narrow::BM) * (H / Narrow::BNS);
+  t.tpe[1] = (H / WideGU::BM) * (F / WideGU::BNS);
+  // Tall tiles: whole ones, bf16 (fp32 gradients leave from the accumulators,
+  // which tall tiles were not measured with), and at least four tall tiles per
+  // workgroup: with three (16 experts, H = 2048, F = 768) the gate/up
+  // gradients took 91 us against 88 on 128-row tiles.
+  constexpr int kMin = 4 * kPlanWgs;
+  t.tall[0] = !dw_f32 && H % Tall::BN == 0 && F % Tall::BM == 0 && E * (t.tpe[0] / 2) >= kMin;
+  t.tall[1] = !dw_f32 && H % TallGU::BM == 0 && E * (t.tpe[1] / 2) >= kMin;
+  return t;
 }
 
 hipError_t launch_gateup_fwd(const ExpertArgs& a, hipStream_t s, bool recompute) {
@@ -931,10 +980,9 @@ hipError_t launch_gateup_dgrad(const ExpertArgs& a, const bf16_t* dg, const bf16
 hipError_t launch_experts_bwd_data(const ExpertArgs& a, const bf16_t* d_o, bf16_t* dg, bf16_t* du,
                                    bf16_t* dxp, void* dw_down, bool dw_f32, hipStream_t s) {
   if (!a.wgrad_plan_built) {
-    int tpe_down = 0, tpe_gu = 0;
-    wgrad_tiles_per_expert(a.H, a.F, tpe_down, tpe_gu);
     TraceScope trace_scope(K_WGRAD_PLAN, s);
-    hipLaunchKernelGGL(k_wgrad_plan, dim3(1), dim3(256), 0, s, a.offsets, a.E, tpe_down, tpe_gu, a.wgrad_plan);
+    hipLaunchKernelGGL(k_wgrad_plan, dim3(1), dim3(256), 0, s, a.offsets, a.E, wgrad_tiles(a.E, a.H, a.F, dw_f32),
+                       a.wgrad_plan);
   }
   if (a.F % 256 == 0) down_dgrad<Wide>(a, d_o, dg, du, nullptr, s);
   else down_dgrad<Narrow>(a, d_o, dg, du, nullptr, s);

@@ -39,18 +39,18 @@ typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef uint32_t v4u32 __attribute__((ext_vector_type(4)));
 #define MOE_LDS __attribute__((address_space(3)))
 
-// BM x BN tile computed by WM x WN waves (each (BM/WM) x (BN/WN)).
-template <int BM_, int BN_, int NB_, int WM_ = 2, int WN_ = 2>
+// BM x BN tile computed by WM x WN waves (each (BM/WM) x (BN/WN)) in K steps of KB.
+template <int BM_, int BN_, int NB_, int WM_ = 2, int WN_ = 2, int KB_ = BK>
 struct Tile {
-  static constexpr int BM = BM_, BN = BN_, NB = NB_, WM = WM_, WN = WN_;
+  static constexpr int BM = BM_, BN = BN_, NB = NB_, WM = WM_, WN = WN_, KB = KB_;
   static constexpr int kThreads = 64 * WM * WN;
   static constexpr int FM = BM / WM / 16;  // 16-row A fragments per wave
   static constexpr int FN = BN / WN / 16;  // 16-row B fragments per wave
   static constexpr int BNS = BN / NB;      // rows of one B operand in the tile
-  static constexpr int kABytes = BM * BK * 2;
-  static constexpr int kBBytes = BN * BK * 2;
+  static constexpr int kABytes = BM * KB * 2;
+  static constexpr int kBBytes = BN * KB * 2;
   static constexpr int kStage = kABytes + kBBytes;
-  static constexpr int kLds = 2 * kStage;
+    static constexpr int kLds = 2 * kStage;
 };
 
 // ---------------------------------------------------------------- LDS layouts
@@ -144,11 +144,11 @@ struct LoadKc {
 // MN-contiguous operand: ROWS columns of the tile's [64][TROWS] LDS layout
 // starting at column `col0`.  Columns >= r_lim (a multiple of 8) and k >= K
 // read as zero.
-template <int ROWS, int TROWS, int kThreads>
+template <int ROWS, int TROWS, int kThreads, int KB>
 struct LoadMn {
   static constexpr int kUnits = ROWS / 8;  // 16-byte units per k-row
-  static constexpr int kPer = BK * kUnits / kThreads;
-  static_assert(kPer * kThreads == BK * kUnits, "tile columns must split evenly over the threads");
+  static constexpr int kPer = KB * kUnits / kThreads;
+  static_assert(kPer * kThreads == KB * kUnits, "tile columns must split evenly over the threads");
   const char* base;
   int64_t valid;  // bytes of the K valid k-rows
   int32_t ld2;    // row pitch in bytes
@@ -166,7 +166,7 @@ struct LoadMn {
   }
   __device__ __forceinline__ void disable() { valid = 0; }
   __device__ __forceinline__ void load(uint4 (&v)[kPer], int kt, int, int) const {
-    const int64_t step = static_cast<int64_t>(kt) * BK * ld2;  // 64-bit: K rows can span more than 2^31 bytes
+    const int64_t step = static_cast<int64_t>(kt) * KB * ld2;  // 64-bit: K rows can span more than 2^31 bytes
     const __amdgpu_buffer_rsrc_t r = make_rsrc(base + step, valid - step);
 #pragma unroll
     for (int i = 0; i < kPer; ++i) v[i] = buf_load16(r, off[i]);
@@ -181,14 +181,15 @@ struct LoadMn {
   }
 };
 
-template <bool KC, int ROWS, int TROWS, int NT>
+template <bool KC, int ROWS, int TROWS, int NT, int KB>
 struct Loader : LoadKc<ROWS, NT> {
+  static_assert(KB == BK, "K-contiguous tiles are 64 deep");
   __device__ __forceinline__ void setup(const bf16_t* src, int64_t ld, int r_lim, int, int tid) {
     this->init(src, ld, r_lim, tid);
   }
 };
-template <int ROWS, int TROWS, int NT>
-struct Loader<false, ROWS, TROWS, NT> : LoadMn<ROWS, TROWS, NT> {
+template <int ROWS, int TROWS, int NT, int KB>
+struct Loader<false, ROWS, TROWS, NT, KB> : LoadMn<ROWS, TROWS, NT, KB> {
   __device__ __forceinline__ void setup(const bf16_t* src, int64_t ld, int r_lim, int K, int tid) {
     this->init(src, ld, r_lim, K, tid);
   }
@@ -218,6 +219,23 @@ __device__ __forceinline__ uint4 frag(const char* lds, int rbase, int ks, int la
     const uint2 a = __builtin_bit_cast(uint2, lo), b = __builtin_bit_cast(uint2, hi);
     return make_uint4(a.x, a.y, b.x, b.y);
   }
+}
+
+// The MN-contiguous fragment in two parts: this lane's byte offset in the
+// tile, and the read (k and k + 4 share the swizzle).
+template <int TROWS>
+__device__ __forceinline__ int frag_mn_off(int rbase, int ks, int lane) {
+  const int s = lane & 15, g = lane >> 4;
+  const int n = rbase + 4 * (s & 3);
+  return mn_off<TROWS>(ks * 32 + 8 * g + (s >> 2), n >> 3) + (n & 7) * 2;
+}
+template <int TROWS>
+__device__ __forceinline__ uint4 frag_mn_at(const char* at) {
+  const MOE_LDS char* p = (const MOE_LDS char*)(at);
+  const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MOE_LDS v4i16*)(p));
+  const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MOE_LDS v4i16*)(p + 4 * TROWS * 2));
+  const uint2 a = __builtin_bit_cast(uint2, lo), b = __builtin_bit_cast(uint2, hi);
+  return make_uint4(a.x, a.y, b.x, b.y);
 }
 
 // First B-tile row of wave column wn's fragment ni.  With NB = 2 the first
@@ -290,8 +308,8 @@ __device__ __forceinline__ void gemm_mainloop(const bf16_t* a, int64_t lda, int 
                                               const bf16_t* const* b, int64_t ldb, int n_lim, int K,
                                               char* smem, f32x4 (&acc)[C::FM][C::FN],
                                               const int32_t* a_rows = nullptr, int64_t a_bytes = 0) {
-  using LA = Loader<A_KC, C::BM, C::BM, C::kThreads>;
-  using LB = Loader<B_KC, C::BNS, C::BN, C::kThreads>;
+  using LA = Loader<A_KC, C::BM, C::BM, C::kThreads, C::KB>;
+  using LB = Loader<B_KC, C::BNS, C::BN, C::kThreads, C::KB>;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave / C::WN, wn = wave % C::WN;
@@ -445,7 +463,13 @@ struct Job {
 template <class C>
 struct Staged {
   static constexpr int kRowBytes = C::BN * 2;                         // one tile row, all NB blocks
-  static constexpr int kBytes = C::BM * kRowBytes;                    // LDS staging area
+  // Rows of the staging area.  A tile too tall for the LDS that its two
+  // stages leave stages and stores its last rows (kTailRows) first.
+  static constexpr int kFit = (160 * 1024 - C::kLds) / kRowBytes;
+  static constexpr int kRows = C::BM <= kFit ? C::BM : kFit;
+  static constexpr int kTailRows = C::BM - kRows;
+  static constexpr int kBytes = kRows * kRowBytes;                    // LDS staging area
+  static_assert(kTailRows <= kRows && kTailRows % 16 == 0 && kRows % 16 == 0, "the tail fits the staging area");
   static constexpr int kXor = (C::BN / 8 < 16 ? C::BN / 8 : 16) - 1;  // rows of 16 hit distinct banks
   static __device__ __forceinline__ int off(int r, int q) { return r * kRowBytes + ((q ^ (r & kXor)) << 4); }
 };
@@ -514,7 +538,10 @@ struct StagedCopy {
   static constexpr int kRowsPerWave = 64 / kCpr;
   static constexpr int kSliceRows = C::kThreads / 64 / C::NB * kRowsPerWave;
   static constexpr int kSlices = C::BM / kSliceRows;
-  static constexpr int kCalls = kSlices / 2;  // two slices per drain call
+  static constexpr int kRowSlices = SO::kRows / kSliceRows;  // slices of the staging area; the rest are the tail's
+  static constexpr bool kSplit = C::KB != BK;                // one slice per drain call instead of two
+  static constexpr int kCalls = kSplit ? kRowSlices : kRowSlices / 2;
+  static_assert(kRowSlices * kSliceRows == SO::kRows && kRowSlices % 2 == 0, "whole calls");
   static_assert(64 % kCpr == 0 && (C::kThreads / 64) % C::NB == 0, "a wave stores whole block rows of one block");
   static_assert(kSlices * kSliceRows == C::BM && kSlices % 2 == 0 && kSliceRows % 16 == 0,
                 "an even number of slices of 16k rows (the swizzle repeats every 16 rows)");
@@ -534,19 +561,45 @@ struct StagedCopy {
     d.out = rows_rsrc(o, rows, ld * 2, C::BNS * 2);
     d.ld = static_cast<uint32_t>(ld * 2);
   }
-  __device__ static __forceinline__ void slice(const State& d, const char* stg, int sl) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int cq = lane % kCpr;
+  __device__ static __forceinline__ uint4 read(const State&, const char* stg, int sl) {
+    const int t = thread();
+    const int lane = t & 63, wv = t >> 6;
     const int row0 = (wv / C::NB) * kRowsPerWave + lane / kCpr;  // row within the slice
-    const int s = sl < kSlices ? sl : kSlices - 1;
-    const uint4 v = *reinterpret_cast<const uint4*>(stg + SO::off(row0, (wv % C::NB) * kCpr + cq) +
-                                                    s * (kSliceRows * SO::kRowBytes));
-    const uint32_t off = static_cast<uint32_t>(row0 + s * kSliceRows) * d.ld + cq * 16;
-    buf_store16<kKeep>(d.out, sl < kSlices ? off : kOob, v);
+    const int s = sl < kRowSlices ? sl : kRowSlices - 1;
+    return *reinterpret_cast<const uint4*>(stg + SO::off(row0, (wv % C::NB) * kCpr + lane % kCpr) +
+                                           s * (kSliceRows * SO::kRowBytes));
   }
-  __device__ static __forceinline__ void call(const State& d, const char* stg, int p) {  // two slices
-    slice(d, stg, 2 * p);
-    slice(d, stg, 2 * p + 1);
+  // row `first` + the slice's: the staging area's rows (first = 0) or the tail's
+  __device__ static __forceinline__ void write(const State& d, const uint4& v, int sl, int first = 0) {
+    const int t = thread();
+    const int lane = t & 63, wv = t >> 6;
+    const int row = (wv / C::NB) * kRowsPerWave + lane / kCpr + first + sl * kSliceRows;
+    // past the last slice the offset is out of range (an OR, not a branch that would split the step)
+    const uint32_t past = sl < kRowSlices ? 0u : kOob;
+    buf_store16<kKeep>(d.out, (static_cast<uint32_t>(row) * d.ld + (lane % kCpr) * 16) | past, v);
+  }
+  // The thread index; in the half-step pipeline opaque, so that per-lane
+  // offsets are recomputed where they are used instead of held in registers.
+  __device__ static __forceinline__ int thread() {
+    int t = threadIdx.x;
+    if constexpr (C::KB != BK) asm volatile("" : "+v"(t));
+    return t;
+  }
+  __device__ static __forceinline__ void slice(const State& d, const char* stg, int sl) {
+    write(d, read(d, stg, sl), sl);
+  }
+  // the tail's slices, staged in the area's first rows
+  __device__ static __forceinline__ void tail(const State& d, const char* stg) {
+#pragma unroll
+    for (int s = 0; s < SO::kTailRows / kSliceRows; ++s) write(d, read(d, stg, s), s, SO::kRows);
+  }
+  __device__ static __forceinline__ void call(const State& d, const char* stg, int p) {
+    if constexpr (kSplit) {
+      slice(d, stg, p);
+    } else {
+      slice(d, stg, 2 * p);
+      slice(d, stg, 2 * p + 1);
+    }
   }
 };
 
@@ -567,6 +620,7 @@ struct StagedCopyOut {
     Copy::setup(d, dst, ld, rows);
   }
   __device__ __forceinline__ void drain(Drain& d, const char* stg, int p) const { Copy::call(d, stg, p); }
+  __device__ __forceinline__ void drain_tail(Drain& d, const char* stg) const { Copy::tail(d, stg); }
   __device__ __forceinline__ void drain_reset(Drain& d) const { Copy::reset(d); }
 };
 
@@ -593,8 +647,10 @@ template <class C, bool A_KC, bool B_KC, class P>
 __device__ __forceinline__ void gemm_stream(const P& prov, char* smem) {
   static_assert(std::is_same<C, typename P::C>::value, "the provider's tile shape");
   constexpr bool kStaged = staged_provider<P>::value;
-  using LA = Loader<A_KC, C::BM, C::BM, C::kThreads>;
-  using LB = Loader<B_KC, C::BNS, C::BN, C::kThreads>;
+  constexpr bool kShallow = C::KB != BK;  // one 32-deep slice per stage
+  static_assert(!kShallow || (C::KB == 32 && !A_KC && !B_KC && C::FM % 2 == 0), "shallow tiles are MN-contiguous");
+  using LA = Loader<A_KC, C::BM, C::BM, C::kThreads, C::KB>;
+  using LB = Loader<B_KC, C::BNS, C::BN, C::kThreads, C::KB>;
   using S0 = std::integral_constant<int, 0>;
   using S1 = std::integral_constant<int, 1>;
   const int tid = threadIdx.x;
@@ -620,7 +676,7 @@ __device__ __forceinline__ void gemm_stream(const P& prov, char* smem) {
       // per-lane offsets are recomputed at each job instead of being held
       // (and spilled) across the whole stream
       int t = tid;
-      if constexpr (opaque_setup<P>::value) asm volatile("" : "+v"(t));
+      if constexpr (opaque_setup<P>::value || kShallow) asm volatile("" : "+v"(t));
       la.setup(lj.a, lj.lda, lj.m_lim, lj.K, t);
 #pragma unroll
       for (int i = 0; i < C::NB; ++i) lb[i].setup(lj.b[i], lj.ldb, lj.n_lim, lj.K, t);
@@ -638,7 +694,7 @@ __device__ __forceinline__ void gemm_stream(const P& prov, char* smem) {
     for (int i = 0; i < C::NB; ++i) lb[i].load(rb[S][i], lkt, lj.K, tid);
   };
   auto lnext = [&]() {
-    if (lok && ++lkt * BK >= lj.K) {
+    if (lok && ++lkt * C::KB >= lj.K) {
       lkt = 0;
       lok = prov.get(++li, lj);
       lsettle();
@@ -665,23 +721,41 @@ __device__ __forceinline__ void gemm_stream(const P& prov, char* smem) {
     if constexpr (kStaged)
       for (; d_call < kCalls; ++d_call) prov.drain(dr, stg, d_call);
   };
+  // writes the finished tile's rows [lo, hi) (multiples of 16) into the staging area from its first row on
+  auto stage_rows = [&](int lo, int hi) {
+    int t = tid;
+    if constexpr (kShallow) asm volatile("" : "+v"(t));
+    const int w_ = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wm_ = w_ / C::WN, wn_ = w_ % C::WN, l_ = t & 63;
+#pragma unroll
+    for (int mi = 0; mi < C::FM; ++mi) {
+      const int r0 = wm_ * (C::BM / C::WM) + mi * 16;
+      if constexpr (Staged<C>::kTailRows > 0) {
+        if (r0 < lo || r0 >= hi) continue;
+      }
+      const int r = r0 - lo + (l_ & 15);
+#pragma unroll
+      for (int ni = 0; ni < C::FN; ++ni) {
+        const int c = brow<C>(wn_, ni) + 4 * (l_ >> 4);
+        *reinterpret_cast<uint2*>(stg + Staged<C>::off(r, c >> 3) + (c & 7) * 2) = pack4_bf16(acc[mi][ni]);
+      }
+    }
+  };
   auto finish = [&](const Job<C>& j) {  // a finished tile: epilogue, or into the staging area
     if constexpr (kStaged) {
       if (d_call < kCalls) {  // the previous tile is not fully drained yet (short K)
         drain_rest();
         lds_barrier();
       }
-      const int wm_ = (tid >> 6) / C::WN;
-#pragma unroll
-      for (int mi = 0; mi < C::FM; ++mi) {
-        const int r = wm_ * (C::BM / C::WM) + mi * 16 + (lane & 15);
-#pragma unroll
-        for (int ni = 0; ni < C::FN; ++ni) {
-          const int c = frag_col<C>(ni, lane);
-          *reinterpret_cast<uint2*>(stg + Staged<C>::off(r, c >> 3) + (c & 7) * 2) = pack4_bf16(acc[mi][ni]);
-        }
-      }
       prov.drain_setup(j, dr);
+      constexpr int kRows = Staged<C>::kRows;
+      if constexpr (Staged<C>::kTailRows > 0) {
+        stage_rows(kRows, C::BM);
+        lds_barrier();
+        prov.drain_tail(dr, stg);
+        lds_barrier();
+      }
+      stage_rows(0, kRows);
       d_call = 0;
       lds_barrier();
     } else {
@@ -704,7 +778,7 @@ __device__ __forceinline__ void gemm_stream(const P& prov, char* smem) {
   };
   csettle();
   auto cadvance = [&]() {
-    if (++ckt * BK >= cj.K) {
+    if (++ckt * C::KB >= cj.K) {
       ckt = 0;
       if (!cj.chain) {
         finish(cj);
@@ -756,6 +830,54 @@ __device__ __forceinline__ void gemm_stream(const P& prov, char* smem) {
     lnext();
   };
 
+  // The step of tiles with one 32-deep slice per stage.  The A fragments are
+  // read in two halves, so that the MFMAs start once the B and the first A
+  // fragments are there.  Fragment addresses differ from the first one's in
+  // bits that neither the lane nor the swizzle's row part carries into, so each
+  // is one XOR away from it; made opaque, the XORs stay where they are used
+  // (held for every fragment they are 12 registers that the accumulators need).
+  auto step32 = [&](auto set) {
+    constexpr int S = decltype(set)::value;
+    using Other = std::integral_constant<int, 1 - S>;
+    const char* cur = smem + S * C::kStage;
+    char* nxt = smem + (1 - S) * C::kStage;
+    constexpr int kHM = C::FM / 2;
+    // one drain call a step while the staged tile lasts, behind a branch: a
+    // store that is issued for nothing costs a step as much as one of its loads
+    if (d_call < kCalls) {
+      drain_next();
+      ++d_call;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    uint4 a0[kHM], a1[kHM], b0[C::FN];
+    int a_at = frag_mn_off<C::BM>(wm * (C::BM / C::WM), 0, lane);
+    int b_at = C::kABytes + frag_mn_off<C::BN>(brow<C>(wn, 0), 0, lane);
+    asm volatile("" : "+v"(a_at), "+v"(b_at));
+#pragma unroll
+    for (int ni = 0; ni < C::FN; ++ni) b0[ni] = frag_mn_at<C::BN>(cur + (b_at ^ (brow<C>(0, ni) * 2)));
+#pragma unroll
+    for (int mi = 0; mi < kHM; ++mi) a0[mi] = frag_mn_at<C::BM>(cur + (a_at ^ (mi * 32)));
+#pragma unroll
+    for (int mi = 0; mi < kHM; ++mi) a1[mi] = frag_mn_at<C::BM>(cur + (a_at ^ ((kHM + mi) * 32)));
+#pragma unroll
+    for (int mi = 0; mi < C::FM; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < C::FN; ++ni)
+        acc[mi][ni] = mfma16x16x32(b0[ni], mi < kHM ? a0[mi % kHM] : a1[mi % kHM], acc[mi][ni]);
+    store(Other{}, nxt);
+    load(Other{});
+    constexpr int kFirst = 2 * C::FN + 4;  // B and two A fragments
+    __builtin_amdgcn_sched_group_barrier(0x100, kFirst, 0);
+    interleave<kMfma / 2, kReads - kFirst, 0x100, 0, 0x200>();
+    interleave<kMfma / 2, kWrites, 0x200, kLoads, 0x020>();
+    lds_barrier();
+    lnext();
+  };
+  auto run_step = [&](auto set) {
+    if constexpr (kShallow) step32(set);
+    else step(set);
+  };
+
   if (!cok) {  // only empty jobs: the last of them may still be staged
     drain_rest();
     return;
@@ -775,9 +897,9 @@ __device__ __forceinline__ void gemm_stream(const P& prov, char* smem) {
   // after S0 left an edge to the loop head that skipped S1, and S0 waited
   // for loads issued one step earlier instead of two).
   for (;;) {  // cok holds here (checked above)
-    step(S0{});
+    run_step(S0{});
     cadvance();
-    step(S1{});
+    run_step(S1{});
     if (!cok) break;
     cadvance();
     if (!cok) break;

@@ -67,10 +67,16 @@ struct ExpertArgs {
 };
 
 int max_row_tiles(int rows_cap, int E);
-// Ints of the weight gradients' schedule (ExpertArgs::wgrad_plan), and the
-// tiles per expert of the down and gate/up weight gradients it schedules.
+// Ints of the weight gradients' schedule (ExpertArgs::wgrad_plan), and what
+// it schedules: the 128-row tiles per expert of the down (0) and gate/up (1)
+// weight gradients, and whether each may run on 256-row tiles instead (the
+// plan decides, from the rows per expert).
 int wgrad_plan_ints(int E);
-void wgrad_tiles_per_expert(int H, int F, int& tpe_down, int& tpe_gu);
+struct WgradTiles {
+  int tpe[2] = {0, 0};
+  bool tall[2] = {false, false};
+};
+WgradTiles wgrad_tiles(int E, int H, int F, bool dw_f32);
 // Column blocks of the down product's dgrad (the dgate_part row length).
 int dgate_parts(int F);
 
@@ -158,7 +164,7 @@ hipError_t launch_combine(const bf16_t* o, const float* gates, const int32_t* ro
 // schedule from `offsets` (E experts, tiles per expert of H x F gradients).
 hipError_t launch_combine_bwd(const bf16_t* dy, const float* gates, const int32_t* row_of, int T, int H, int k,
                               bf16_t* d_o, hipStream_t s, const int32_t* offsets = nullptr, int E = 0, int F = 0,
-                              int32_t* plan = nullptr);
+                              bool dw_f32 = false, int32_t* plan = nullptr);
 // After the down product's dgrad (which leaves part[r][0..nparts), the inner
 // products <dA[r], A[r]> per column block): dg = <dY[t], O[row]> = sum / g,
 // dz per slot (fp32 [T,k]) and dense over E (bf16 [T,E]).  With a non-zero

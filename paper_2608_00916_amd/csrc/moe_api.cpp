@@ -479,7 +479,7 @@ int moe_bwd(const moe_dims* d, const void* x, const void* w_r, const void* w_gat
   const bool f32 = d->flags & MOE_F_DW_FP32;
   // the combine backward's extra workgroup also builds the weight gradients' schedule
   hipError_t e = launch_combine_bwd(static_cast<const bf16_t*>(dy), sv.gates, sv.row_of, T, H, k, w.d_o, s,
-                                    sv.offsets, E, F, w.plan);
+                                    sv.offsets, E, F, f32, w.plan);
   if (e != hipSuccess) return hip_status(e, "combine bwd");
   ExpertArgs a{T * k, H, E, F, sv.xp, static_cast<const bf16_t*>(w_gate), static_cast<const bf16_t*>(w_up),
                static_cast<const bf16_t*>(w_down), sv.offsets, sv.tile_start, sv.tile_desc, sv.g, sv.u, sv.a};

@@ -12,23 +12,42 @@
 // XCDs, so its rows are fetched into few L2s.  Each tile is still computed
 // whole by one workgroup: the schedule changes no result.
 //
+// Tile height.  A weight gradient that may (WgradTiles::tall) runs on
+// 256 x 256 tiles, half as many: at 128 experts x 512 rows, H = 2048, F = 768
+// the down product took 246-250 us against 276 with 128 x 256, the gate/up
+// product 536-542 against 555.  It stays on 128-row tiles where the longest
+// tile is more than half of a workgroup's mean work, as halving the tile count
+// then costs more in balance (hottest expert at 10x the mean, T = 32768: the
+// down product 1010 us against 970; at 0.39 of the mean work, the gate/up
+// product 1870 against 1950).
+//
 // Layout (wgrad_plan_ints(E) ints): plan[0, E) the expert at each position of
 // the order; then, per weight gradient q (0: down, 1: gate/up), the first
-// tile of XCD x at plan[E + q (kPlanXcds + 1) + x], x = 0..kPlanXcds.
+// tile of XCD x at plan[E + q (kPlanXcds + 1) + x], x = 0..kPlanXcds; then
+// per q whether its tiles are tall (plan_tall).
 #pragma once
 
 #include "common.hpp"
+#include "launch.hpp"
 #include "moe.h"
 
 namespace moe {
 
 constexpr int kPlanXcds = 8;
 constexpr int kPlanBK = 64;    // K steps are 64 rows deep
+constexpr int kPlanWgs = 256;   // workgroups of the persistent grid (one per CU)
 constexpr int kTileFixed = 2;  // a tile's fixed cost (setup, epilogue) in K steps
 
-// One workgroup of 256 threads (E <= 256) builds the plan; tpe0 / tpe1 are the
-// tiles per expert of the down and gate/up weight gradients.
-__device__ __forceinline__ void build_wgrad_plan(const int32_t* __restrict__ offsets, int E, int tpe0, int tpe1,
+__host__ __device__ constexpr int plan_tall(int E, int q) { return E + 2 * (kPlanXcds + 1) + q; }
+
+// Whether weight gradient q runs on tall tiles: `longest` and `total` are the
+// work of the longest tile and of one tile of every expert.
+__device__ __forceinline__ bool use_tall(const WgradTiles& t, int q, int longest, int64_t total) {
+  return t.tall[q] && 2LL * kPlanWgs * longest <= t.tpe[q] / 2 * total;
+}
+
+// One workgroup of 256 threads (E <= 256) builds the plan.
+__device__ __forceinline__ void build_wgrad_plan(const int32_t* __restrict__ offsets, int E, const WgradTiles& tiles,
                                                  int32_t* __restrict__ plan) {
   static_assert(MOE_MAX_EXPERTS <= 256, "one thread per expert");
   constexpr int kPairs = 2 * (kPlanXcds + 1);
@@ -73,6 +92,13 @@ __device__ __forceinline__ void build_wgrad_plan(const int32_t* __restrict__ off
   const int cum = before + incl - v;  // work of the positions before tid, per tile of each
   if (tid < E) cum_at[tid] = cum;
   const int total = wave_tot[0] + wave_tot[1] + wave_tot[2] + wave_tot[3];
+  const bool tall0 = use_tall(tiles, 0, steps_at[0], total), tall1 = use_tall(tiles, 1, steps_at[0], total);
+  const int tpe0 = tall0 ? tiles.tpe[0] / 2 : tiles.tpe[0];
+  const int tpe1 = tall1 ? tiles.tpe[1] / 2 : tiles.tpe[1];
+  if (tid == 0) {
+    plan[plan_tall(E, 0)] = tall0;
+    plan[plan_tall(E, 1)] = tall1;
+  }
   if (tid < kPairs) {
     const int q = tid / (kPlanXcds + 1), x = tid % (kPlanXcds + 1);
     const int64_t tpe = q == 0 ? tpe0 : tpe1;

@@ -98,3 +98,50 @@ def test_recompute_is_bit_identical():
             assert ex.views["g"] is None and ex.views["u"] is None
     for n in outs[0]:
         assert np.array_equal(outs[0][n], outs[1][n]), n
+
+
+def test_tall_weight_gradient_tiles():
+    """Enough tiles for the 256-row weight-gradient tiles, with rows per expert
+    around their 32-row steps (down to none): parity with the oracle on one
+    expert of each count, and every expert's gradients bitwise those of a run
+    whose one long expert sends the plan to the 128-row tiles (both sum the
+    rows in the same order)."""
+    import torch
+    import paper_2608_00916_amd as moe
+    E, H, F = 256, 512, 512
+    kinds = [0, 1, 31, 32, 33, 64, 65, 95]
+    counts = np.array(kinds * (E // len(kinds)), dtype=np.int32)
+    counts[-1] = 40
+    rows = int(counts.sum()) + 8192
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    t = {n: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g) for n, shape, std in (
+        ("xp", (rows, H), 1.0), ("wg", (E, H, F), 0.02), ("wu", (E, H, F), 0.02), ("wd", (E, F, H), 0.02),
+        ("d_o", (rows, H), 1.0))}
+    ex = moe.MoEExperts(rows, H, E, F)
+    grads = []
+    for last in (40, 40 + 8192):
+        c = counts.copy()
+        c[-1] = last
+        print(f"GPU experts tall rows={int(c.sum())} H={H} E={E} F={F} last={last}", flush=True)
+        ex.forward(t["xp"], torch.from_numpy(c).cuda(), t["wg"], t["wu"], t["wd"])
+        ex.backward(t["xp"], t["wg"], t["wu"], t["wd"], t["d_o"])
+        torch.cuda.synchronize()
+        grads.append([w.clone() for w in (ex.dw_gate, ex.dw_up, ex.dw_down)])
+    for a, b in zip(*grads):
+        assert torch.equal(a[:-1], b[:-1])
+        assert not torch.equal(a[-1], b[-1])
+    ends = np.cumsum(counts)
+    for e in range(len(kinds)):
+        n = int(counts[e])
+        if n == 0:
+            assert not any(w[e].any() for w in grads[0])
+            continue
+        sl = slice(int(ends[e]) - n, int(ends[e]))
+        w = {m: host(v[e:e + 1]) for m, v in t.items() if m in ("wg", "wu", "wd")}
+        x, d_o = host(t["xp"][sl]), host(t["d_o"][sl])
+        one = np.array([n])
+        f = O.experts_share_forward(x, one, w["wg"], w["wu"], w["wd"])
+        b = O.experts_share_backward(x, one, w["wg"], w["wu"], w["wd"], f, d_o)
+        for m, got in zip(("dw_gate", "dw_up", "dw_down"), grads[0]):
+            assert_close(f"{m}[{e}]", host(got[e]), b[m][0], 2e-2)
