@@ -297,3 +297,13 @@ def test_router_losses(case):
     assert np.abs(b["dw_r"] - b0["dw_r"]).max() > 0.5 * np.abs(b0["dw_r"]).max()
     assert_close("dx", g["dx"], b["dx"], case="router_losses_" + case)
     assert_close("dw_r", g["dw_r"], b["dw_r"], case="router_losses_" + case)
+
+
+@pytest.mark.parametrize("T", [1024, 1025])
+def test_router_split_count_edge(T):
+    """Either side of the token count at which the router's K split changes
+    (H not a multiple of either split, so some ranges are empty), k over one
+    register batch of the permutation, a last chunk of one token."""
+    inp = workloads.block_inputs(T=T, H=1152, E=24, k=12, F=128, seed=31)
+    f, b = oracle_run(inp)
+    compare(inp, gpu_run(inp), f, b, case=f"router_split_T{T}")
