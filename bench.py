@@ -79,7 +79,7 @@ def short_kernel_name(name):
                 "DownFwd": "down_fwd", "DownDgrad": "down_dgrad_swiglu", "GateUpDgrad": "gateup_dgrad",
                 "LoraWgrad": "lora_wgrad"}.get(m.group(1), m.group(1))
         # the adapter (rank-r) variants of the row-grouped products
-        lora = re.search(r"(?:Fwd|Dgrad)Jobs<(?:[^<>]*<[^<>]*>, )?true>", name) is not None
+        lora = re.search(r"(?:Fwd|Dgrad)Jobs<(?:[^<>]*<[^<>]*>, )?true[,>]", name) is not None
         return base + ("_lora" if lora else "")
     m = re.search(r"k_(\w+?)(?:<|\(|$)", name)
     if m:

@@ -100,12 +100,12 @@ __global__ __launch_bounds__(LoraRows::kThreads) void k_lora_rows(
     // channels: the four products of a rank-16 step took 218 us so, 190-192
     // with this stride, 205 with one step, 192-195 with 3, 5 or 7.
     const int first = (m0 / C::BM * 2) % cdiv(K, BK);
-    gemm_mainloop<C, true, B_KC, true>(x0 + static_cast<int64_t>(m0) * ldx, ldx, m_lim, b0, ldw, C::BN, K, smem, acc, nullptr,
-                                 0, first);
+    gemm_mainloop<C, true, B_KC, true>(x0 + static_cast<int64_t>(m0) * ldx, ldx, m_lim, b0, ldw, C::BN, K, smem, acc,
+                                       nullptr, 0, first);
     if constexpr (NSEG == 2) {
       const bf16_t* b1[1] = {w1 + wofs};
       gemm_mainloop<C, true, B_KC, true>(x1 + static_cast<int64_t>(m0) * ldx, ldx, m_lim, b1, ldw, C::BN, K, smem, acc,
-                                   nullptr, 0, first);
+                                         nullptr, 0, first);
     }
     const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -520,10 +520,13 @@ __device__ __forceinline__ uint4 pack8(const float (&f)[8]) {
 }
 
 // G, U (gate/up products) and A = silu(G) U per expert, with the SwiGLU on the
-// bf16 G and U; G and U are skipped when g_out is null, A when a_out is.
+// bf16 G and U.  kOut says what is stored: a store through an empty resource
+// costs its issue all the same (T = 8192, H = 2048, F = 768: A alone 525 -> 510
+// us, G and U alone 526 -> 516 us without the stores that wrote nothing).
 // With kLora a second segment P1 [b1_gate | b1_up][e] (P1 = scale Xp a1,
 // [rows][r]; b1 [E][r][F], MN-contiguous like W_gate).
-template <bool kLora>
+enum GateUpOut { kOutAll, kOutA, kOutGU };  // A alone: a forward that will recompute; G and U alone: the recompute
+template <bool kLora, GateUpOut kOut>
 struct GateUpFwdJobs {
   static constexpr bool kOpaqueSetup = kLora;  // short of registers with the adapter segment
   using C = GateUpFwd;
@@ -588,10 +591,11 @@ struct GateUpFwdJobs {
 #pragma unroll
     for (int i = 0; i < 8; ++i) av[i] = silu_f(gv[i]) * uv[i];
     const uint32_t off = sl < Units::kSlices ? static_cast<uint32_t>(r * F * 2 + c * 16) : kOob;
-    const int rows_gu = g_out != nullptr ? d.rows : 0, rows_a = a_out != nullptr ? d.rows : 0;
-    buf_store16(rows_rsrc(g_out + d.base, rows_gu, F * 2, C::BNS * 2), off, gw);
-    buf_store16(rows_rsrc(u_out + d.base, rows_gu, F * 2, C::BNS * 2), off, uw);
-    buf_store16(rows_rsrc(a_out + d.base, rows_a, F * 2, C::BNS * 2), off, pack8(av));
+    if constexpr (kOut != kOutA) {
+      buf_store16(rows_rsrc(g_out + d.base, d.rows, F * 2, C::BNS * 2), off, gw);
+      buf_store16(rows_rsrc(u_out + d.base, d.rows, F * 2, C::BNS * 2), off, uw);
+    }
+    if constexpr (kOut != kOutGU) buf_store16(rows_rsrc(a_out + d.base, d.rows, F * 2, C::BNS * 2), off, pack8(av));
   }
 };
 
@@ -803,6 +807,20 @@ void run_stream(const P& prov, int64_t max_jobs, int kid, hipStream_t s) {
   hipLaunchKernelGGL(k, dim3(grid), dim3(P::C::kThreads), 0, s, prov);
 }
 
+template <bool kLora, GateUpOut kOut>
+void gateup_fwd_out(const ExpertArgs& a, const LoraSeg& lo, int64_t tiles, int kid, hipStream_t s) {
+  run_stream<true, false>(GateUpFwdJobs<kLora, kOut>{a.xp, a.w_gate, a.w_up, a.tile_start, a.tile_desc, a.E, a.H, a.F,
+                                                     a.g, a.u, a.act, lo},
+                          tiles, kid, s);
+}
+
+template <bool kLora>
+void gateup_fwd(const ExpertArgs& a, const LoraSeg& lo, int64_t tiles, int kid, hipStream_t s) {
+  if (a.g == nullptr) gateup_fwd_out<kLora, kOutA>(a, lo, tiles, kid, s);
+  else if (a.act == nullptr) gateup_fwd_out<kLora, kOutGU>(a, lo, tiles, kid, s);
+  else gateup_fwd_out<kLora, kOutAll>(a, lo, tiles, kid, s);
+}
+
 template <class C>
 void down_fwd(const ExpertArgs& a, bf16_t* o, hipStream_t s) {
   LoraSeg lo;
@@ -954,14 +972,8 @@ hipError_t launch_gateup_fwd(const ExpertArgs& a, hipStream_t s, bool recompute)
     lo.b1 = a.lora.b1_up;
     lo.rank = a.lora.rank;
   }
-  if (lo.rank > 0)
-    run_stream<true, false>(GateUpFwdJobs<true>{a.xp, a.w_gate, a.w_up, a.tile_start, a.tile_desc, a.E, a.H, a.F, a.g,
-                                                a.u, a.act, lo},
-                            tiles, kid, s);
-  else
-    run_stream<true, false>(GateUpFwdJobs<false>{a.xp, a.w_gate, a.w_up, a.tile_start, a.tile_desc, a.E, a.H, a.F,
-                                                 a.g, a.u, a.act, lo},
-                            tiles, kid, s);
+  if (lo.rank > 0) gateup_fwd<true>(a, lo, tiles, kid, s);
+  else gateup_fwd<false>(a, lo, tiles, kid, s);
   return hipGetLastError();
 }
 
