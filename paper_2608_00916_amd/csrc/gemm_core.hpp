@@ -1,6 +1,7 @@
 // bf16 MFMA GEMM core shared by every matrix product of the MoE block.
 //
-// One workgroup (WM x WN waves of 64 lanes) computes a BM x BN fp32 tile C = A_tile * B_tile over a K loop in steps of BK = 64:
+// One workgroup (WM x WN waves of 64 lanes) computes a BM x BN fp32 tile
+// C = A_tile * B_tile over a K loop in steps of BK = 64 (32 for tall tiles of MN-contiguous operands):
 //   C[m][n] = sum_k A(m, k) B(k, n)
 // Operands come from global memory in one of two layouts:
 //   K-contiguous   element (r, k) at src[r * ld + k]   (a row-major A, or B^T)
@@ -50,7 +51,7 @@ struct Tile {
   static constexpr int kABytes = BM * KB * 2;
   static constexpr int kBBytes = BN * KB * 2;
   static constexpr int kStage = kABytes + kBBytes;
-    static constexpr int kLds = 2 * kStage;
+  static constexpr int kLds = 2 * kStage;
 };
 
 // ---------------------------------------------------------------- LDS layouts
@@ -464,7 +465,8 @@ struct Job {
 //   drain(Drain&, staging, p)      call p (p >= kDrainCalls: no memory effect)
 //   drain_reset(Drain&)            a state whose calls touch no memory
 // A tile whose successor is shorter than kDrainCalls step pairs is drained
-// in full before the successor is staged.
+// in full before the successor is staged.  Tiles of 32-deep steps (KB = 32) get
+// a drain call in every step.
 // Staging layout: tile row r (BN bf16, all NB blocks side by side), 16-byte
 // chunk q at Staged<C>::off(r, q).
 template <class C>
@@ -585,7 +587,7 @@ struct StagedCopy {
     const uint32_t past = sl < kRowSlices ? 0u : kOob;
     buf_store16<kKeep>(d.out, (static_cast<uint32_t>(row) * d.ld + (lane % kCpr) * 16) | past, v);
   }
-  // The thread index; in the half-step pipeline opaque, so that per-lane
+  // The thread index; for tiles of 32-deep steps opaque, so that per-lane
   // offsets are recomputed where they are used instead of held in registers.
   __device__ static __forceinline__ int thread() {
     int t = threadIdx.x;
