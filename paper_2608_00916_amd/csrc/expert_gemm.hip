@@ -94,18 +94,15 @@ __global__ __launch_bounds__(LoraRows::kThreads) void k_lora_rows(
     const int64_t wofs = static_cast<int64_t>(t.e) * estride + (B_KC ? static_cast<int64_t>(q0) * K : q0);
     const int64_t ldw = B_KC ? K : rank;
     const bf16_t* b0[1] = {w0 + wofs};
-    // Waves start their sums two steps (256 bytes) apart.  All starting at
-    // step 0 they read the same 128 bytes of every row at about the same time,
-    // and rows a multiple of 4 KB apart (H = 2048) then share few memory
-    // channels: the four products of a rank-16 step took 218 us so, 190-192
-    // with this stride, 205 with one step, 192-195 with 3, 5 or 7.
-    const int first = (m0 / C::BM * 2) % cdiv(K, BK);
-    gemm_mainloop<C, true, B_KC, true>(x0 + static_cast<int64_t>(m0) * ldx, ldx, m_lim, b0, ldw, C::BN, K, smem, acc,
-                                       nullptr, 0, first);
+    // Every sum goes up in K, wherever the row lies: a row's P and Q must not
+    // depend on the rows before it.  Waves that started at K steps apart by
+    // their place (rows a multiple of 4 KB apart, H = 2048, otherwise share few
+    // memory channels) took 190 us instead of 218 for the four products of a
+    // rank-16 step, but rounded a token's row by where its batch put it.
+    gemm_mainloop<C, true, B_KC>(x0 + static_cast<int64_t>(m0) * ldx, ldx, m_lim, b0, ldw, C::BN, K, smem, acc);
     if constexpr (NSEG == 2) {
       const bf16_t* b1[1] = {w1 + wofs};
-      gemm_mainloop<C, true, B_KC, true>(x1 + static_cast<int64_t>(m0) * ldx, ldx, m_lim, b1, ldw, C::BN, K, smem, acc,
-                                         nullptr, 0, first);
+      gemm_mainloop<C, true, B_KC>(x1 + static_cast<int64_t>(m0) * ldx, ldx, m_lim, b1, ldw, C::BN, K, smem, acc);
     }
     const int lane = threadIdx.x & 63;
 #pragma unroll

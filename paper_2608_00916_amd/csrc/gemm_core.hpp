@@ -302,16 +302,13 @@ __device__ __forceinline__ void interleave() {
 //   n_lim  valid columns of each B operand (multiple of 8)
 //   a_rows if non-null (K-contiguous A only), tile row r is row a_rows[r] of
 //          the matrix at `a`, whose a_bytes (< 2^31) bound every access
-//   first_step  with kWrap the K step the sum starts at, 0 <= first_step <
-//          K steps; it wraps around
 // Software pipeline: global loads run two K steps ahead of the MFMAs in two
 // register sets; LDS holds two stages; one LDS barrier per step.
-template <class C, bool A_KC, bool B_KC, bool kWrap = false>
+template <class C, bool A_KC, bool B_KC>
 __device__ __forceinline__ void gemm_mainloop(const bf16_t* a, int64_t lda, int m_lim,
                                               const bf16_t* const* b, int64_t ldb, int n_lim, int K,
                                               char* smem, f32x4 (&acc)[C::FM][C::FN],
-                                              const int32_t* a_rows = nullptr, int64_t a_bytes = 0,
-                                              int first_step = 0) {
+                                              const int32_t* a_rows = nullptr, int64_t a_bytes = 0) {
   using LA = Loader<A_KC, C::BM, C::BM, C::kThreads, C::KB>;
   using LB = Loader<B_KC, C::BNS, C::BN, C::kThreads, C::KB>;
   const int tid = threadIdx.x;
@@ -334,10 +331,6 @@ __device__ __forceinline__ void gemm_mainloop(const bf16_t* a, int64_t lda, int 
 
   auto load = [&](auto set, int kt) {
     constexpr int S = decltype(set)::value;
-    if constexpr (kWrap) {
-      const int wrapped = kt + first_step - (kt + first_step >= nk ? nk : 0);
-      kt = kt < nk ? wrapped : nk;  // a step past the end stays past it
-    }
     la.load(ra[S], kt, K, tid);
 #pragma unroll
     for (int i = 0; i < C::NB; ++i) lb[i].load(rb[S][i], kt, K, tid);

@@ -118,6 +118,21 @@ def test_lora_recompute_is_bit_identical():
         assert np.array_equal(a[n], r[n]), n
 
 
+@pytest.mark.parametrize("rank", [16, 48])
+def test_lora_rows_do_not_depend_on_their_place(rank):
+    """Y and dX of a token are the same bits when its batch is run alone and
+    when other tokens come before it, which moves its rows to other places of
+    the experts' row tiles.  Every sum over H, F and rank goes up in K whatever
+    tile or half of a tile a row lies in, so nothing may differ."""
+    n_before, T = 77, 377
+    inp = workloads.block_inputs(T=T, H=512, E=8, k=2, F=384, seed=69)
+    lo, scale = lora_inputs(inp, rank, seed=169)
+    alone = dict(inp, dims=dict(inp["dims"], T=T - n_before), x=inp["x"][n_before:], dy=inp["dy"][n_before:])
+    a, b = run(alone, rank, lo, scale), run(inp, rank, lo, scale)
+    for n in ("logits", "idx", "gates", "y", "dx"):
+        assert np.array_equal(a[n], b[n][n_before:]), n
+
+
 def test_lora_with_router_losses():
     """The frozen router still passes its input gradient, including the
     router losses' part, into dX."""
