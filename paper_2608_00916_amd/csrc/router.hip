@@ -3,8 +3,6 @@
 // softmax-over-selection gates.
 #include <math.h>
 
-#include <algorithm>
-
 #include "gemm_core.hpp"
 #include "launch.hpp"
 #include "trace.hpp"
@@ -16,7 +14,7 @@ namespace {
 static_assert(MOE_MAX_EXPERTS <= 4 * kWave, "at most four experts per lane in the top-k");
 
 // Logits z = x W_r, fp32 [T][E], split over K: workgroup (i, s) multiplies
-// tokens 128 i .. 128 i + 127 by W_r over the s-th of router_splits(T)
+// tokens 128 i .. 128 i + 127 by W_r over the s-th of kRouterSplits
 // contiguous K ranges (whole 64-deep steps) and writes its partial sums,
 // split 0 into `logits` and split s > 0 into part[s - 1] ([T][E] each); the
 // top-k kernel adds them in split order.  All E experts per workgroup, one
@@ -27,15 +25,12 @@ static_assert(MOE_MAX_EXPERTS <= 4 * kWave, "at most four experts per lane in th
 // while W_r is read T / 128 times instead of T / 32.
 using RouterTile = Tile<128, 128, 1, 2, 2>;
 constexpr int kRouterTokens = RouterTile::BM;
-constexpr int kRouterSplits = 4, kRouterSplitsSmall = 16;
-constexpr int kRouterSmallT = 1024;
-// Few tokens leave most of the chip idle and the K steps of one workgroup are
-// the kernel's time: 16 ranges (2 steps each at H = 2048) instead of 4 took
-// 8.6-9.8 us against 12.8-13.4 at T = 64 and 512, and the top-k, which adds
-// the partial sums, 0.6-0.9 us more.  From T = 4096 on 4 ranges fill the chip.
-__host__ __device__ constexpr int router_splits(int T) {
-  return T <= kRouterSmallT ? kRouterSplitsSmall : kRouterSplits;
-}
+// One count for every T: it is the order in which a token's logits are summed,
+// and a passage must select the same experts alone and inside a batch.  16
+// ranges up to T = 1024, where few tokens leave most of the chip idle, took
+// 8.8 us against 12.9 at T = 64 (the top-k 1 us more), but a token's logits
+// then differed in their last bits on either side of that T.
+constexpr int kRouterSplits = 4;
 
 __global__ __launch_bounds__(RouterTile::kThreads) void k_router_logits(const bf16_t* __restrict__ x,
                                                                         const bf16_t* __restrict__ w_r, int T,
@@ -50,8 +45,7 @@ __global__ __launch_bounds__(RouterTile::kThreads) void k_router_logits(const bf
   const int t0 = blockIdx.x * kRouterTokens;
   const int rows = min(kRouterTokens, T - t0);
   const int split = blockIdx.y;
-  const int kper =
-      (T <= kRouterSmallT ? cdiv(cdiv(H, kRouterSplitsSmall), BK) : cdiv(cdiv(H, kRouterSplits), BK)) * BK;
+  const int kper = cdiv(cdiv(H, kRouterSplits), BK) * BK;
   const int k0 = min(H, split * kper);
   const int kn = min(H, k0 + kper) - k0;  // 0 for an empty split: its partial sums are zeros
   float* out = split == 0 ? logits : part + static_cast<int64_t>(split - 1) * T * E;
@@ -194,14 +188,8 @@ __global__ __launch_bounds__(256) void k_topk(float* __restrict__ logits, const 
       float v = 0.0f;
       if (e < E) {
         v = z[e];
-        const float* p = part + static_cast<int64_t>(t) * E + e;
-        if (T <= kRouterSmallT) {
 #pragma unroll
-          for (int sp = 0; sp < kRouterSplitsSmall - 1; ++sp) v += p[sp * plane];
-        } else {
-#pragma unroll
-          for (int sp = 0; sp < kRouterSplits - 1; ++sp) v += p[sp * plane];
-        }
+        for (int sp = 0; sp < kRouterSplits - 1; ++sp) v += part[sp * plane + static_cast<int64_t>(t) * E + e];
         z[e] = v;
       }
       val[m] = v;
@@ -295,18 +283,14 @@ __global__ __launch_bounds__(256) void k_router_loss_final(const float* __restri
 }  // namespace
 
 int64_t router_loss_ws_floats(int T, int E) { return static_cast<int64_t>(cdiv(T, 4)) * (E + 1) + E + 1; }
-int64_t router_part_floats(int T, int E) {
-  // monotonic in T: never less than a smaller T needs: a workspace for T tokens serves fewer too
-  const int64_t small = static_cast<int64_t>(kRouterSplitsSmall - 1) * std::min(T, kRouterSmallT);
-  return std::max(small, static_cast<int64_t>(kRouterSplits - 1) * T) * E;
-}
+int64_t router_part_floats(int T, int E) { return static_cast<int64_t>(kRouterSplits - 1) * T * E; }
 
 hipError_t launch_router_fwd(const bf16_t* x, const bf16_t* w_r, const uint8_t* mask, int T, int H,
                              int E, int k, float* logits, float* part, int32_t* topk_idx, float* gates,
                              float* aux_ws, int32_t* chunk_counts, int32_t* row_token, hipStream_t s) {
   {
     TraceScope trace_scope(K_ROUTER_LOGITS, s);
-    hipLaunchKernelGGL(k_router_logits, dim3(cdiv(T, kRouterTokens), router_splits(T)), dim3(RouterTile::kThreads), 0,
+    hipLaunchKernelGGL(k_router_logits, dim3(cdiv(T, kRouterTokens), kRouterSplits), dim3(RouterTile::kThreads), 0,
                        s, x, w_r, T, H, E, logits, part, chunk_counts, static_cast<int>(permute_ws_ints(T, E)));
   }
   {

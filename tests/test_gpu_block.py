@@ -300,10 +300,29 @@ def test_router_losses(case):
 
 
 @pytest.mark.parametrize("T", [1024, 1025])
-def test_router_split_count_edge(T):
-    """Either side of the token count at which the router's K split changes
-    (H not a multiple of either split, so some ranges are empty), k over one
-    register batch of the permutation, a last chunk of one token."""
+def test_token_count_edge(T):
+    """Whole chunks and tiles of tokens, and a last chunk of one token; k over
+    one register batch of the permutation (H = 1152: K ranges of the router of
+    unequal length)."""
     inp = workloads.block_inputs(T=T, H=1152, E=24, k=12, F=128, seed=31)
     f, b = oracle_run(inp)
-    compare(inp, gpu_run(inp), f, b, case=f"router_split_T{T}")
+    compare(inp, gpu_run(inp), f, b, case=f"token_count_T{T}")
+
+
+@pytest.mark.parametrize("T,n_before", [(1024, 1), (64, 961), (1000, 1000)])
+def test_tokens_do_not_depend_on_the_batch_size(T, n_before):
+    """A token's logits, selection, gates, Y (training and serving pass) and dX
+    are the same bits in a batch of T tokens and in one of n_before + T: every
+    product sums K in one order for any number of tokens."""
+    import torch
+    import paper_2608_00916_amd as moe
+    inp = workloads.block_inputs(T=n_before + T, H=1152, E=24, k=12, F=128, seed=33)
+    part = dict(inp, dims=dict(inp["dims"], T=T), x=inp["x"][n_before:], dy=inp["dy"][n_before:])
+    a, b = gpu_run(part), gpu_run(inp)
+    for n in ("logits", "topk_idx", "gates", "y", "dx"):
+        assert np.array_equal(a[n], b[n][n_before:]), n
+    d = part["dims"]
+    inf = moe.MoEInfer(d["T"], d["H"], d["E"], d["F"], d["k"])
+    inf.forward(*(dev_bf16(part[n]) for n in ("x", "w_r", "w_gate", "w_up", "w_down")))
+    torch.cuda.synchronize()
+    assert np.array_equal(host(inf.y), a["y"])
