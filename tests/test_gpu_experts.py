@@ -100,16 +100,28 @@ def test_recompute_is_bit_identical():
         assert np.array_equal(outs[0][n], outs[1][n]), n
 
 
+def tall_flags(ex):
+    """Whether the down and the gate/up weight gradients of the last backward
+    ran on 256-row tiles.  The schedule is the last region of the experts'
+    workspace: the experts in their order, 2 x 9 tile bounds, the two flags."""
+    n = ex.d.E + 2 * 9 + 2
+    start = ex.ws.numel() - -(-n * 4 // 256) * 256
+    plan = ex.ws[start:start + n * 4].cpu().numpy().view(np.int32)
+    assert np.array_equal(np.sort(plan[:ex.d.E]), np.arange(ex.d.E)), "not the schedule"
+    return bool(plan[-2]), bool(plan[-1])
+
+
 def test_tall_weight_gradient_tiles():
     """Enough tiles for the 256-row weight-gradient tiles, with rows per expert
-    around their 32-row steps (down to none): parity with the oracle on one
-    expert of each count, and every expert's gradients bitwise those of a run
-    whose one long expert sends the plan to the 128-row tiles (both sum the
-    rows in the same order)."""
+    around their 32-row steps, down to none and up to more steps (14) than a
+    staged tile has drain calls (12): parity with the oracle on one expert of
+    each count, and every expert's gradients bitwise those of a run whose one
+    long expert sends the plan to the 128-row tiles (both sum the rows in the
+    same order).  The plan's flags say which tiles either run took."""
     import torch
     import paper_2608_00916_amd as moe
     E, H, F = 256, 512, 512
-    kinds = [0, 1, 31, 32, 33, 64, 65, 95]
+    kinds = [0, 1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 200, 385, 416, 417, 417]
     counts = np.array(kinds * (E // len(kinds)), dtype=np.int32)
     counts[-1] = 40
     rows = int(counts.sum()) + 8192
@@ -120,13 +132,14 @@ def test_tall_weight_gradient_tiles():
         ("d_o", (rows, H), 1.0))}
     ex = moe.MoEExperts(rows, H, E, F)
     grads = []
-    for last in (40, 40 + 8192):
+    for last, tall in ((40, True), (40 + 8192, False)):
         c = counts.copy()
         c[-1] = last
         print(f"GPU experts tall rows={int(c.sum())} H={H} E={E} F={F} last={last}", flush=True)
         ex.forward(t["xp"], torch.from_numpy(c).cuda(), t["wg"], t["wu"], t["wd"])
         ex.backward(t["xp"], t["wg"], t["wu"], t["wd"], t["d_o"])
         torch.cuda.synchronize()
+        assert tall_flags(ex) == (tall, tall)
         grads.append([w.clone() for w in (ex.dw_gate, ex.dw_up, ex.dw_down)])
     for a, b in zip(*grads):
         assert torch.equal(a[:-1], b[:-1])
