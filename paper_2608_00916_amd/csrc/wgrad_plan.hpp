@@ -15,11 +15,20 @@
 // Tile height.  A weight gradient that may (WgradTiles::tall) runs on
 // 256 x 256 tiles, half as many: at 128 experts x 512 rows, H = 2048, F = 768
 // the down product took 246-250 us against 276 with 128 x 256, the gate/up
-// product 536-542 against 555.  It stays on 128-row tiles where the longest
-// tile is more than half of a workgroup's mean work, as halving the tile count
-// then costs more in balance (hottest expert at 10x the mean, T = 32768: the
-// down product 1010 us against 970; at 0.39 of the mean work, the gate/up
-// product 1870 against 1950).
+// product 536-542 against 555.  It stays on 128-row tiles
+//  * where the longest tile is more than half of a workgroup's mean work, as
+//    halving the tile count then costs more in balance (hottest expert at 10x
+//    the mean, T = 32768: the down product 1010 us against 970; at 0.39 of the
+//    mean work, the gate/up product 1870 against 1950);
+//  * for a mean of 25 to 41 rows per expert: many experts then take two 32-row
+//    steps where 128-row tiles take one of 64 rows (same widths, gate/up: 171
+//    us against 180 at 24 rows, 2-4% slower at 26 to 40, 2% faster at 42);
+//  * with fewer than 8 tall tiles per workgroup also for any mean under 48:
+//    the stores of a tile's last 64 rows, which nothing overlaps, then weigh
+//    more (down product at 8 rows, 256 experts: 512 x 512, 4 per workgroup, 41 us
+//    against 36; 512 x 768, 6 per workgroup, 8% slower; 1024 x 512, 8 per
+//    workgroup, even; at 42 rows 7% and 4% slower, 5% faster).
+// The order of the experts and the XCDs' shares count 64-row steps for either height.
 //
 // Layout (wgrad_plan_ints(E) ints): plan[0, E) the expert at each position of
 // the order; then, per weight gradient q (0: down, 1: gate/up), the first
@@ -37,13 +46,21 @@ constexpr int kPlanXcds = 8;
 constexpr int kPlanBK = 64;    // K steps are 64 rows deep
 constexpr int kPlanWgs = 256;   // workgroups of the persistent grid (one per CU)
 constexpr int kTileFixed = 2;  // a tile's fixed cost (setup, epilogue) in K steps
+// Tile height (above): mean rows per expert up to which and from which on tiles
+// are tall, with kTallMany of them per workgroup and with fewer.
+constexpr int kTallMany = 8;
+constexpr int kTallShallow = 24, kTallDeepMany = 42, kTallDeepFew = 48;
 
 __host__ __device__ constexpr int plan_tall(int E, int q) { return E + 2 * (kPlanXcds + 1) + q; }
 
 // Whether weight gradient q runs on tall tiles: `longest` and `total` are the
-// work of the longest tile and of one tile of every expert.
-__device__ __forceinline__ bool use_tall(const WgradTiles& t, int q, int longest, int64_t total) {
-  return t.tall[q] && 2LL * kPlanWgs * longest <= t.tpe[q] / 2 * total;
+// work of the longest tile and of one tile of every expert, `rows` the rows of
+// all E experts.
+__device__ __forceinline__ bool use_tall(const WgradTiles& t, int q, int E, int rows, int longest, int64_t total) {
+  const int tpe = t.tpe[q] / 2;
+  const bool many = E * tpe >= kTallMany * kPlanWgs;
+  const bool depth = many ? rows <= kTallShallow * E || rows >= kTallDeepMany * E : rows >= kTallDeepFew * E;
+  return t.tall[q] && depth && 2LL * kPlanWgs * longest <= tpe * total;
 }
 
 // One workgroup of 256 threads (E <= 256) builds the plan.
@@ -92,7 +109,9 @@ __device__ __forceinline__ void build_wgrad_plan(const int32_t* __restrict__ off
   const int cum = before + incl - v;  // work of the positions before tid, per tile of each
   if (tid < E) cum_at[tid] = cum;
   const int total = wave_tot[0] + wave_tot[1] + wave_tot[2] + wave_tot[3];
-  const bool tall0 = use_tall(tiles, 0, steps_at[0], total), tall1 = use_tall(tiles, 1, steps_at[0], total);
+  const int all_rows = offsets[E] - offsets[0];
+  const bool tall0 = use_tall(tiles, 0, E, all_rows, steps_at[0], total);
+  const bool tall1 = use_tall(tiles, 1, E, all_rows, steps_at[0], total);
   const int tpe0 = tall0 ? tiles.tpe[0] / 2 : tiles.tpe[0];
   const int tpe1 = tall1 ? tiles.tpe[1] / 2 : tiles.tpe[1];
   if (tid == 0) {

@@ -158,3 +158,26 @@ def test_tall_weight_gradient_tiles():
         b = O.experts_share_backward(x, one, w["wg"], w["wu"], w["wd"], f, d_o)
         for m, got in zip(("dw_gate", "dw_up", "dw_down"), grads[0]):
             assert_close(f"{m}[{e}]", host(got[e]), b[m][0], 2e-2)
+
+
+@pytest.mark.parametrize("H,n,flags", [
+    (1024, 0, (True, True)), (1024, 24, (True, True)), (1024, 25, (False, False)), (1024, 41, (False, False)),
+    (1024, 42, (True, True)), (768, 24, (False, True)), (768, 25, (False, False)), (768, 47, (False, True)),
+    (768, 48, (True, True))])
+def test_tall_tiles_follow_rows_per_expert(H, n, flags):
+    """The plan takes 256-row tiles up to a mean of 24 rows per expert and from
+    42 on, with fewer than 8 of them per workgroup from 48 on only (E = 256,
+    F = 512: down and gate/up have 8 and 16 of them at H = 1024, 6 and 12 at
+    H = 768)."""
+    import torch
+    import paper_2608_00916_amd as moe
+    E, F = 256, 512
+    print(f"GPU experts tall rule H={H} E={E} F={F} n={n}", flush=True)
+    rows = E * n + 1
+    w = [torch.zeros(E, a, b, dtype=torch.bfloat16, device="cuda") for a, b in ((H, F), (H, F), (F, H))]
+    x = torch.zeros(rows, H, dtype=torch.bfloat16, device="cuda")
+    ex = moe.MoEExperts(rows, H, E, F)
+    ex.forward(x, torch.full((E,), n, dtype=torch.int32, device="cuda"), *w)
+    ex.backward(x, *w, x)
+    torch.cuda.synchronize()
+    assert tall_flags(ex) == flags
