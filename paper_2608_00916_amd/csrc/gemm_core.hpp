@@ -580,15 +580,30 @@ struct StagedCopy {
     const uint32_t past = sl < kRowSlices ? 0u : kOob;
     buf_store16<kKeep>(d.out, (static_cast<uint32_t>(row) * d.ld + (lane % kCpr) * 16) | past, v);
   }
-  // The thread index; for tiles of 32-deep steps opaque, so that per-lane
-  // offsets are recomputed where they are used instead of held in registers.
+  // The thread index, opaque, so that per-lane offsets are recomputed where
+  // they are used instead of held in registers.
   __device__ static __forceinline__ int thread() {
     int t = threadIdx.x;
-    if constexpr (C::KB != BK) asm volatile("" : "+v"(t));
+    asm volatile("" : "+v"(t));
     return t;
   }
+  // read, write and tail are for tiles of 32-deep steps.  Those of 64-deep steps
+  // have code of their own here and where tiles are staged (gemm_stream): with
+  // code shared by both heights their streams took longer (T = 8192, H = 1920,
+  // F = 640: down product 300 us against 294, its dgrad 336 against 329).
   __device__ static __forceinline__ void slice(const State& d, const char* stg, int sl) {
-    write(d, read(d, stg, sl), sl);
+    if constexpr (kSplit) {
+      write(d, read(d, stg, sl), sl);
+    } else {
+      const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+      const int cq = lane % kCpr;
+      const int row0 = (wv / C::NB) * kRowsPerWave + lane / kCpr;  // row within the slice
+      const int s = sl < kSlices ? sl : kSlices - 1;
+      const uint4 v = *reinterpret_cast<const uint4*>(stg + SO::off(row0, (wv % C::NB) * kCpr + cq) +
+                                                      s * (kSliceRows * SO::kRowBytes));
+      const uint32_t off = static_cast<uint32_t>(row0 + s * kSliceRows) * d.ld + cq * 16;
+      buf_store16<kKeep>(d.out, sl < kSlices ? off : kOob, v);
+    }
   }
   // the tail's slices, staged in the area's first rows
   __device__ static __forceinline__ void tail(const State& d, const char* stg) {
@@ -723,18 +738,16 @@ __device__ __forceinline__ void gemm_stream(const P& prov, char* smem) {
     if constexpr (kStaged)
       for (; d_call < kCalls; ++d_call) prov.drain(dr, stg, d_call);
   };
-  // writes the finished tile's rows [lo, hi) (multiples of 16) into the staging area from its first row on
+  // writes rows [lo, hi) (multiples of 16) of a tile too tall for the staging area into it from its first row on
   auto stage_rows = [&](int lo, int hi) {
     int t = tid;
-    if constexpr (kShallow) asm volatile("" : "+v"(t));
-    const int w_ = kShallow ? __builtin_amdgcn_readfirstlane(t >> 6) : t >> 6;
+    asm volatile("" : "+v"(t));
+    const int w_ = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm_ = w_ / C::WN, wn_ = w_ % C::WN, l_ = t & 63;
 #pragma unroll
     for (int mi = 0; mi < C::FM; ++mi) {
       const int r0 = wm_ * (C::BM / C::WM) + mi * 16;
-      if constexpr (Staged<C>::kTailRows > 0) {
-        if (r0 < lo || r0 >= hi) continue;
-      }
+      if (r0 < lo || r0 >= hi) continue;
       const int r = r0 - lo + (l_ & 15);
 #pragma unroll
       for (int ni = 0; ni < C::FN; ++ni) {
@@ -749,15 +762,27 @@ __device__ __forceinline__ void gemm_stream(const P& prov, char* smem) {
         drain_rest();
         lds_barrier();
       }
-      prov.drain_setup(j, dr);
-      constexpr int kRows = Staged<C>::kRows;
       if constexpr (Staged<C>::kTailRows > 0) {
+        constexpr int kRows = Staged<C>::kRows;
+        prov.drain_setup(j, dr);
         stage_rows(kRows, C::BM);
         lds_barrier();
         prov.drain_tail(dr, stg);
         lds_barrier();
+        stage_rows(0, kRows);
+      } else {  // set up last: a drain's first loads (G and U) would hold registers during the staging
+        const int wm_ = (tid >> 6) / C::WN;
+#pragma unroll
+        for (int mi = 0; mi < C::FM; ++mi) {
+          const int r = wm_ * (C::BM / C::WM) + mi * 16 + (lane & 15);
+#pragma unroll
+          for (int ni = 0; ni < C::FN; ++ni) {
+            const int c = frag_col<C>(ni, lane);
+            *reinterpret_cast<uint2*>(stg + Staged<C>::off(r, c >> 3) + (c & 7) * 2) = pack4_bf16(acc[mi][ni]);
+          }
+        }
+        prov.drain_setup(j, dr);
       }
-      stage_rows(0, kRows);
       d_call = 0;
       lds_barrier();
     } else {
@@ -875,10 +900,6 @@ __device__ __forceinline__ void gemm_stream(const P& prov, char* smem) {
     lds_barrier();
     lnext();
   };
-  auto run_step = [&](auto set) {
-    if constexpr (kShallow) step32(set);
-    else step(set);
-  };
 
   if (!cok) {  // only empty jobs: the last of them may still be staged
     drain_rest();
@@ -899,9 +920,11 @@ __device__ __forceinline__ void gemm_stream(const P& prov, char* smem) {
   // after S0 left an edge to the loop head that skipped S1, and S0 waited
   // for loads issued one step earlier instead of two).
   for (;;) {  // cok holds here (checked above)
-    run_step(S0{});
+    if constexpr (kShallow) step32(S0{});
+    else step(S0{});
     cadvance();
-    run_step(S1{});
+    if constexpr (kShallow) step32(S1{});
+    else step(S1{});
     if (!cok) break;
     cadvance();
     if (!cok) break;
