@@ -23,11 +23,16 @@
 //  * for a mean of 25 to 41 rows per expert: many experts then take two 32-row
 //    steps where 128-row tiles take one of 64 rows (same widths, gate/up: 171
 //    us against 180 at 24 rows, 2-4% slower at 26 to 40, 2% faster at 42);
-//  * with fewer than 8 tall tiles per workgroup also for any mean under 48:
-//    the stores of a tile's last 64 rows, which nothing overlaps, then weigh
-//    more (down product at 8 rows, 256 experts: 512 x 512, 4 per workgroup, 41 us
-//    against 36; 512 x 768, 6 per workgroup, 8% slower; 1024 x 512, 8 per
-//    workgroup, even; at 42 rows 7% and 4% slower, 5% faster).
+//  * for a mean under 3: many experts then have no rows, and their tiles, which take
+//    nearly as long as short ones but count 2 steps against 3 below, leave the
+//    XCDs uneven (1 row: gate/up 10% slower; 192 experts, 1536 x 768, 2 rows: down 5%);
+//  * with fewer than 12 tall tiles per workgroup for any mean under 48: the stores
+//    of a tile's last 64 rows, which nothing overlaps, then weigh more (at 8
+//    rows: 256 experts of 512 x 512, 4 per workgroup, down 41 us against 36;
+//    232 of 256 x 1152, 8 per workgroup, gate/up 9% slower; at 42 rows 7% and 9%).
+// With 8 to 10 per workgroup and H = 256 the gate/up product is up to 6% slower
+// at 56 to 256 rows too, where the last round of tiles is nearly empty, and 3-5%
+// faster from 384 on: the rule does not look at rounds.
 // The order of the experts and the XCDs' shares count 64-row steps for either height.
 //
 // Layout (wgrad_plan_ints(E) ints): plan[0, E) the expert at each position of
@@ -46,10 +51,11 @@ constexpr int kPlanXcds = 8;
 constexpr int kPlanBK = 64;    // K steps are 64 rows deep
 constexpr int kPlanWgs = 256;   // workgroups of the persistent grid (one per CU)
 constexpr int kTileFixed = 2;  // a tile's fixed cost (setup, epilogue) in K steps
-// Tile height (above): mean rows per expert up to which and from which on tiles
-// are tall, with kTallMany of them per workgroup and with fewer.
-constexpr int kTallMany = 8;
-constexpr int kTallShallow = 24, kTallDeepMany = 42, kTallDeepFew = 48;
+// Tile height (above): mean rows per expert from which, up to which and again
+// from which on tiles are tall with kTallMany of them per workgroup, and from
+// which on with fewer.
+constexpr int kTallMany = 12;
+constexpr int kTallFrom = 3, kTallUpTo = 24, kTallAgain = 42, kTallFew = 48;
 
 __host__ __device__ constexpr int plan_tall(int E, int q) { return E + 2 * (kPlanXcds + 1) + q; }
 
@@ -59,7 +65,8 @@ __host__ __device__ constexpr int plan_tall(int E, int q) { return E + 2 * (kPla
 __device__ __forceinline__ bool use_tall(const WgradTiles& t, int q, int E, int rows, int longest, int64_t total) {
   const int tpe = t.tpe[q] / 2;
   const bool many = E * tpe >= kTallMany * kPlanWgs;
-  const bool depth = many ? rows <= kTallShallow * E || rows >= kTallDeepMany * E : rows >= kTallDeepFew * E;
+  const bool depth = rows >= kTallFew * E || (many && (rows >= kTallAgain * E ||
+                                                       (rows >= kTallFrom * E && rows <= kTallUpTo * E)));
   return t.tall[q] && depth && 2LL * kPlanWgs * longest <= tpe * total;
 }
 

@@ -161,14 +161,14 @@ def test_tall_weight_gradient_tiles():
 
 
 @pytest.mark.parametrize("H,n,flags", [
-    (1024, 0, (True, True)), (1024, 24, (True, True)), (1024, 25, (False, False)), (1024, 41, (False, False)),
-    (1024, 42, (True, True)), (768, 24, (False, True)), (768, 25, (False, False)), (768, 47, (False, True)),
-    (768, 48, (True, True))])
+    (1536, 0, (False, False)), (1536, 2, (False, False)), (1536, 3, (True, True)), (1536, 24, (True, True)),
+    (1536, 25, (False, False)), (1536, 41, (False, False)), (1536, 42, (True, True)), (1024, 24, (False, True)),
+    (1024, 25, (False, False)), (1024, 47, (False, True)), (1024, 48, (True, True))])
 def test_tall_tiles_follow_rows_per_expert(H, n, flags):
-    """The plan takes 256-row tiles up to a mean of 24 rows per expert and from
-    42 on, with fewer than 8 of them per workgroup from 48 on only (E = 256,
-    F = 512: down and gate/up have 8 and 16 of them at H = 1024, 6 and 12 at
-    H = 768)."""
+    """The plan takes 256-row tiles for a mean of 3 to 24 rows per expert and
+    from 42 on, with fewer than 12 of them per workgroup from 48 on only (E = 256,
+    F = 512: down and gate/up have 12 and 24 of them at H = 1536, 8 and 16 at
+    H = 1024)."""
     import torch
     import paper_2608_00916_amd as moe
     E, F = 256, 512
