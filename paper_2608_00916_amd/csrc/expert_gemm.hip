@@ -240,6 +240,7 @@ struct DownWgradJobs : StagedCopyOut<C_, DownWgradJobs<C_, F32>> {
     return true;
   }
   static constexpr bool kStaged = !F32;  // bf16 gradients leave through the LDS staging area
+  static constexpr bool kStageByRows = C::BN == 256;
   __device__ void stage_dst(const Job<C>& j, bf16_t* (&dst)[C::NB], int64_t& ld, int& rows) const {
     dst[0] = static_cast<bf16_t*>(dw_down) + static_cast<int64_t>(j.e) * F * H + static_cast<int64_t>(j.m0) * H + j.n0;
     ld = H;
@@ -286,6 +287,7 @@ struct GateUpWgradJobs : StagedCopyOut<C_, GateUpWgradJobs<C_, F32>> {
     return true;
   }
   static constexpr bool kStaged = !F32;
+  static constexpr bool kStageByRows = true;
   __device__ void stage_dst(const Job<C>& j, bf16_t* (&dst)[C::NB], int64_t& ld, int& rows) const {
     const int64_t o = static_cast<int64_t>(j.e) * H * F + static_cast<int64_t>(j.m0) * F + j.n0;
     dst[0] = static_cast<bf16_t*>(dw_gate) + o;
@@ -526,6 +528,7 @@ enum GateUpOut { kOutAll, kOutA, kOutGU };  // A alone: a forward that will reco
 template <bool kLora, GateUpOut kOut>
 struct GateUpFwdJobs {
   static constexpr bool kOpaqueSetup = kLora;  // short of registers with the adapter segment
+  static constexpr bool kStageByRows = true;
   using C = GateUpFwd;
   const bf16_t *xp, *w_gate, *w_up;
   const int32_t* tile_start;

@@ -506,6 +506,19 @@ struct opaque_setup : std::false_type {};
 template <class P>
 struct opaque_setup<P, std::void_t<decltype(P::kOpaqueSetup)>> : std::integral_constant<bool, P::kOpaqueSetup> {};
 
+// A provider that declares `static constexpr bool kStageByRows = true` has its
+// tiles staged by the code of the tall tiles, its drain set up first.  Which of
+// the two a stream does better with is the compiler's register allocation, and
+// measured (T = 8192): by rows the gate/up forward that stores A alone takes 506
+// us against 523 and the tall gate/up weight gradient, which shares its kernel
+// with 128-row tiles, 521 against 524; the other streams lose by it (H = 1920,
+// F = 640: down product 300 against 294, its dgrad, whose first loads of G and U
+// would hold registers during the staging, 336 against 329).
+template <class P, class = void>
+struct stage_by_rows : std::false_type {};
+template <class P>
+struct stage_by_rows<P, std::void_t<decltype(P::kStageByRows)>> : std::integral_constant<bool, P::kStageByRows> {};
+
 // LDS bytes gemm_stream needs for provider P.
 template <class P>
 constexpr int stream_lds() {
@@ -590,10 +603,8 @@ struct StagedCopy {
     asm volatile("" : "+v"(t));
     return t;
   }
-  // read, write and tail are for tiles of 32-deep steps.  Those of 64-deep steps
-  // have code of their own here and where tiles are staged (gemm_stream): with
-  // code shared by both heights their streams took longer (T = 8192, H = 1920,
-  // F = 640: down product 300 us against 294, its dgrad 336 against 329).
+  // read, write and tail are for tiles of 32-deep steps; those of 64-deep steps
+  // take the offset and its select in one expression (stage_by_rows has the times).
   __device__ static __forceinline__ void slice(const State& d, const char* stg, int sl) {
     if constexpr (kSplit) {
       write(d, read(d, stg, sl), sl);
@@ -668,6 +679,7 @@ __device__ __forceinline__ void gemm_stream(const P& prov, char* smem) {
   static_assert(std::is_same<C, typename P::C>::value, "the provider's tile shape");
   constexpr bool kStaged = staged_provider<P>::value;
   constexpr bool kShallow = C::KB != BK;  // one 32-deep slice per stage
+  constexpr bool kByRows = kShallow || stage_by_rows<P>::value;
   static_assert(!kShallow || (C::KB == 32 && !A_KC && !B_KC && C::FM % 2 == 0), "shallow tiles are MN-contiguous");
   using LA = Loader<A_KC, C::BM, C::BM, C::kThreads, C::KB>;
   using LB = Loader<B_KC, C::BNS, C::BN, C::kThreads, C::KB>;
@@ -741,16 +753,18 @@ __device__ __forceinline__ void gemm_stream(const P& prov, char* smem) {
     if constexpr (kStaged)
       for (; d_call < kCalls; ++d_call) prov.drain(dr, stg, d_call);
   };
-  // writes rows [lo, hi) (multiples of 16) of a tile too tall for the staging area into it from its first row on
+  // writes the finished tile's rows [lo, hi) (multiples of 16) into the staging area from its first row on
   auto stage_rows = [&](int lo, int hi) {
     int t = tid;
-    asm volatile("" : "+v"(t));
-    const int w_ = __builtin_amdgcn_readfirstlane(t >> 6);
+    if constexpr (kShallow) asm volatile("" : "+v"(t));
+    const int w_ = kShallow ? __builtin_amdgcn_readfirstlane(t >> 6) : t >> 6;
     const int wm_ = w_ / C::WN, wn_ = w_ % C::WN, l_ = t & 63;
 #pragma unroll
     for (int mi = 0; mi < C::FM; ++mi) {
       const int r0 = wm_ * (C::BM / C::WM) + mi * 16;
-      if (r0 < lo || r0 >= hi) continue;
+      if constexpr (Staged<C>::kTailRows > 0) {
+        if (r0 < lo || r0 >= hi) continue;
+      }
       const int r = r0 - lo + (l_ & 15);
 #pragma unroll
       for (int ni = 0; ni < C::FN; ++ni) {
@@ -765,15 +779,17 @@ __device__ __forceinline__ void gemm_stream(const P& prov, char* smem) {
         drain_rest();
         lds_barrier();
       }
-      if constexpr (Staged<C>::kTailRows > 0) {
+      if constexpr (kByRows) {
         constexpr int kRows = Staged<C>::kRows;
         prov.drain_setup(j, dr);
-        stage_rows(kRows, C::BM);
-        lds_barrier();
-        prov.drain_tail(dr, stg);
-        lds_barrier();
+        if constexpr (Staged<C>::kTailRows > 0) {
+          stage_rows(kRows, C::BM);
+          lds_barrier();
+          prov.drain_tail(dr, stg);
+          lds_barrier();
+        }
         stage_rows(0, kRows);
-      } else {  // set up last: a drain's first loads (G and U) would hold registers during the staging
+      } else {
         const int wm_ = (tid >> 6) / C::WN;
 #pragma unroll
         for (int mi = 0; mi < C::FM; ++mi) {
@@ -904,6 +920,11 @@ __device__ __forceinline__ void gemm_stream(const P& prov, char* smem) {
     lnext();
   };
 
+  auto run_step = [&](auto set) {
+    if constexpr (kShallow) step32(set);
+    else step(set);
+  };
+
   if (!cok) {  // only empty jobs: the last of them may still be staged
     drain_rest();
     return;
@@ -923,10 +944,10 @@ __device__ __forceinline__ void gemm_stream(const P& prov, char* smem) {
   // after S0 left an edge to the loop head that skipped S1, and S0 waited
   // for loads issued one step earlier instead of two).
   for (;;) {  // cok holds here (checked above)
-    if constexpr (kShallow) step32(S0{});
+    if constexpr (kByRows) run_step(S0{});
     else step(S0{});
     cadvance();
-    if constexpr (kShallow) step32(S1{});
+    if constexpr (kByRows) run_step(S1{});
     else step(S1{});
     if (!cok) break;
     cadvance();
