@@ -5,8 +5,8 @@
 // gradients) walk a device-built table of 128-row tiles, so the
 // host never learns the counts: they run as persistent grids (a few workgroups
 // per CU) that stride over the tiles the table holds.  Weight gradients
-// (K = rows of one expert) have a fixed grid of E x (M/128) x (N/128) tiles;
-// experts without rows write zeros.
+// (K = rows of one expert) run over a device-built schedule of tiles of 128 or
+// 256 rows (wgrad_plan.hpp); experts without rows write zeros.
 #include "launch.hpp"
 #include "trace.hpp"
 #include "gemm_core.hpp"

@@ -12,20 +12,30 @@ import bench
 NS = "moe::(anonymous namespace)::"
 
 
+W, N = "moe::Tile<128, 256, 1, 2, 4, 64>", "moe::Tile<128, 128, 1, 2, 2, 64>"
+TALL, WGU, TALLGU = "moe::Tile<256, 256, 1, 2, 4, 32>", "moe::Tile<128, 256, 2, 2, 4, 64>", "moe::Tile<256, 256, 2, 2, 4, 32>"
+
+
 @pytest.mark.parametrize("name,short", [
-    (f"void {NS}k_stream<{NS}GateUpFwdJobs<false>, true, false>({NS}GateUpFwdJobs<false>)", "gateup_fwd"),
-    (f"void {NS}k_stream<{NS}GateUpFwdJobs<true>, true, false>(x)", "gateup_fwd_lora"),
-    (f"void {NS}k_stream<{NS}DownFwdJobs<moe::Tile<128, 256, 1, 2, 4>, false>, true, false>(x)", "down_fwd"),
-    (f"void {NS}k_stream<{NS}DownDgradJobs<moe::Tile<128, 256, 1, 2, 4>, true>, true, true>(x)",
-     "down_dgrad_swiglu_lora"),
-    (f"void {NS}k_stream<{NS}GateUpDgradJobs<moe::Tile<128, 256, 1, 2, 4>, false>, true, true>(x)", "gateup_dgrad"),
-    (f"void {NS}k_stream<{NS}GateUpWgradJobs<moe::Tile<128, 256, 2, 2, 4>, false>, false, false>(x)",
+    (f"void {NS}k_stream<{NS}GateUpFwdJobs<false, ({NS}GateUpOut)0>, true, false>(x)", "gateup_fwd"),
+    (f"void {NS}k_stream<{NS}GateUpFwdJobs<false, ({NS}GateUpOut)1>, true, false>(x)", "gateup_fwd"),
+    (f"void {NS}k_stream<{NS}GateUpFwdJobs<true, ({NS}GateUpOut)0>, true, false>(x)", "gateup_fwd_lora"),
+    (f"void {NS}k_stream<{NS}DownFwdJobs<{W}, false>, true, false>(x)", "down_fwd"),
+    (f"void {NS}k_stream<{NS}DownFwdJobs<{N}, true>, true, false>({NS}DownFwdJobs<{N}, true>)", "down_fwd_lora"),
+    (f"void {NS}k_stream<{NS}DownDgradJobs<{W}, true>, true, true>(x)", "down_dgrad_swiglu_lora"),
+    (f"void {NS}k_stream<{NS}GateUpDgradJobs<{W}, false>, true, true>(x)", "gateup_dgrad"),
+    (f"void {NS}k_stream<{NS}GateUpWgradJobs<{WGU}, true>, false, false>(x)", "gateup_wgrad"),
+    (f"void {NS}k_stream<{NS}DownWgradJobs<{N}, false>, false, false>(x)", "down_wgrad"),
+    (f"void {NS}k_wgrad_stream<{NS}DownWgradJobs<{TALL}, false>, {NS}DownWgradJobs<{W}, false> >(x, x, int const*)",
+     "down_wgrad"),
+    (f"void {NS}k_wgrad_stream<{NS}GateUpWgradJobs<{TALLGU}, false>, {NS}GateUpWgradJobs<{WGU}, false> >(x)",
      "gateup_wgrad"),
-    (f"void {NS}k_stream<{NS}DownWgradJobs<moe::Tile<128, 256, 1, 2, 4>, true>, false, false>(x)", "down_wgrad"),
     (f"void {NS}k_stream<{NS}LoraWgradJobs<false>, false, false>(x)", "lora_wgrad"),
-    (f"void {NS}k_gateup_fwd_rows(unsigned short const*)", "gateup_fwd_rows"),
+    (f"void {NS}k_lora_rows<true, 2>(unsigned short const*)", "lora_rows"),
+    (f"{NS}k_gateup_fwd_rows(unsigned short const*)", "gateup_fwd_rows"),
     (f"void {NS}k_topk<2, false>(float const*)", "topk"),
     (f"void {NS}k_permute_rows<8>(unsigned short const*)", "permute_rows"),
+    (f"{NS}k_wgrad_plan(int const*, int, moe::WgradTiles, int*)", "wgrad_plan"),
 ])
 def test_short_kernel_name(name, short):
     assert bench.short_kernel_name(name) == short
